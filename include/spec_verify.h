@@ -36,8 +36,9 @@
  *   uniforms       [B, gamma+1]     fp32 in [0, 1)
  *   accepted_len   [B]              int32 out, L in [0, gamma]
  *   next_token     [B]              int32 out, in [0, V)
- * Rows need no particular alignment; rows starting at a 4-byte aligned
- * address (every fp32 row, 16-bit rows of even V) are read with 128-bit loads.
+ * Rows need no particular alignment beyond their elements'; they are read
+ * with 128-bit loads wherever they start (16-bit rows of odd V start off a
+ * 4-byte boundary every other row, and stream at about 0.8 of the rate).
  *
  * Ownership and concurrency.  Every pointer is owned by the caller.  The
  * library never allocates device memory and never prints; only

@@ -132,23 +132,17 @@ struct SigmoidWeights {
     }
 };
 
-template <class D>
-__device__ __forceinline__ bool pair_aligned(const typename D::T* rp, const typename D::T* rq, bool two_rows) {
-    const uintptr_t a = reinterpret_cast<uintptr_t>(rp) | (two_rows ? reinterpret_cast<uintptr_t>(rq) : 0);
-    return (a & 3u) == 0;
-}
-
 // Vectors v0 + u * vstride (u < U) from a chunk of n elements of the selected
 // row pair (rp/rq point at the chunk start).  All 16-byte loads are issued
 // before any is used; elements at or beyond n read as -inf (weight 0), and
 // with one row the draft side is -inf.
 template <class D, int U>
 __device__ __forceinline__ void load_pair_u(const typename D::T* rp, const typename D::T* rq, bool two_rows,
-                                            bool fast, int v0, int vstride, int n, float (&zp)[U][D::E],
+                                            int v0, int vstride, int n, float (&zp)[U][D::E],
                                             float (&zq)[U][D::E]) {
     constexpr int E = D::E;
     const int nfull = n / E;
-    if (fast && nfull > 0) {
+    if (nfull > 0) {
         u32x4 a[U], c[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -370,7 +364,7 @@ __device__ __forceinline__ double wave_weight_sum_k(const typename D::T* rp, con
     const int lane = threadIdx.x % kWave;
     const int nvec = (n + E - 1) / E;
     const int nfull = n / E;
-    const bool fast = pair_aligned<D>(rp, rq, two_rows) && nfull > 0;
+    const bool fast = nfull > 0;
     double acc = 0.0;
     for (int v0 = 0; v0 < nvec; v0 += kPassUnroll * kWave) {
         u32x4 ra[kPassUnroll], rb[kPassUnroll];
@@ -438,9 +432,8 @@ __device__ __forceinline__ int sub_chunk_find_k(const typename D::T* rp, const t
     constexpr int NE = NV * E;
     constexpr bool two_rows = (KIND == kResidual);
     const int tid = threadIdx.x;
-    const bool fast = pair_aligned<D>(rp, rq, two_rows);
     float zp[NV][E], zq[NV][E];
-    load_pair_u<D, NV>(rp, rq, two_rows, fast, tid * NV, 1, n, zp, zq);
+    load_pair_u<D, NV>(rp, rq, two_rows, tid * NV, 1, n, zp, zq);
     float a[NE];
     double sum = 0.0;
 #pragma unroll
@@ -505,9 +498,8 @@ __device__ __forceinline__ int wave_sub_chunk_find_k(const typename D::T* rp, co
     constexpr int E = D::E;
     constexpr bool two_rows = (KIND == kResidual);
     const int lane = threadIdx.x % kWave;
-    const bool fast = pair_aligned<D>(rp, rq, two_rows);
     float zp[1][E], zq[1][E];
-    load_pair_u<D, 1>(rp, rq, two_rows, fast, lane, 1, n, zp, zq);
+    load_pair_u<D, 1>(rp, rq, two_rows, lane, 1, n, zp, zq);
     float a[E];
     double sum = 0.0;
 #pragma unroll
@@ -692,22 +684,15 @@ __device__ __forceinline__ void split3(double v, float& hi, float& mid, float& l
 // base, absorbed in blocks of U (all loads of a block issued before any is
 // used, the block sharing one update of the running reference).
 template <int U, class D>
-__device__ __forceinline__ void stats_stream(const typename D::T* base, int nfull, bool aligned, int lane, float c,
-                                             Lse& st) {
+__device__ __forceinline__ void stats_stream(const typename D::T* base, int nfull, int lane, float c, Lse& st) {
     constexpr int E = D::E;
     for (int v0 = 0; v0 < nfull; v0 += U * kWave) {
         float x[U][E];
-        if (aligned) {
-            u32x4 raw[U];
+        u32x4 raw[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) raw[u] = load_vec_or_pad<D, true>(base, v0 + u * kWave + lane, nfull);
+        for (int u = 0; u < U; ++u) raw[u] = load_vec_or_pad<D, true>(base, v0 + u * kWave + lane, nfull);
 #pragma unroll
-            for (int u = 0; u < U; ++u) unpack<D>(raw[u], x[u]);
-        } else {
-            // rows that are not 4-byte aligned (16-bit logits with odd V)
-#pragma unroll
-            for (int u = 0; u < U; ++u) load_elems_or_pad<D>(base, (v0 + u * kWave + lane) * E, nfull * E, x[u]);
-        }
+        for (int u = 0; u < U; ++u) unpack<D>(raw[u], x[u]);
         lse_absorb_block<U, E>(st, x, c);
     }
 }
@@ -751,7 +736,6 @@ __device__ __forceinline__ void stats_role(const StepParams& P, int b, int slot,
     const T* base = row + sp.begin;
     const int n = sp.n;
     const int nfull = n / E;  // whole vectors of E elements
-    const bool aligned = vec_loadable(base);
 
     // Lane l takes whole vectors l, l + 64, ... of the quarter in blocks of
     // kUnroll; all loads of a block are issued before any is used, and the
@@ -765,30 +749,15 @@ __device__ __forceinline__ void stats_role(const StepParams& P, int b, int slot,
         // chunks hold one or two per lane)
         const int per_lane = (nfull + kWave - 1) / kWave;
         if (per_lane <= 1)
-            stats_stream<1, D>(base, nfull, aligned, lane, c, st);
+            stats_stream<1, D>(base, nfull, lane, c, st);
         else if (per_lane <= 2)
-            stats_stream<2, D>(base, nfull, aligned, lane, c, st);
+            stats_stream<2, D>(base, nfull, lane, c, st);
         else if (per_lane <= 4)
-            stats_stream<4, D>(base, nfull, aligned, lane, c, st);
+            stats_stream<4, D>(base, nfull, lane, c, st);
         else
-            stats_stream<kUnroll, D>(base, nfull, aligned, lane, c, st);
+            stats_stream<kUnroll, D>(base, nfull, lane, c, st);
     } else {
-        for (int v0 = 0; v0 < nfull; v0 += kUnroll * kWave) {
-            float x[kUnroll][E];
-            if (aligned) {
-                u32x4 raw[kUnroll];
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) raw[u] = load_vec_or_pad<D, true>(base, v0 + u * kWave + lane, nfull);
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u) unpack<D>(raw[u], x[u]);
-            } else {
-                // rows that are not 4-byte aligned (16-bit logits with odd V)
-#pragma unroll
-                for (int u = 0; u < kUnroll; ++u)
-                    load_elems_or_pad<D>(base, (v0 + u * kWave + lane) * E, nfull * E, x[u]);
-            }
-            lse_absorb_block<kUnroll, E>(st, x, c);
-        }
+        stats_stream<kUnroll, D>(base, nfull, lane, c, st);
     }
     if (n > nfull * E && lane == nfull % kWave) {
         float x[1][E];
@@ -1562,9 +1531,8 @@ __device__ __forceinline__ int wave_find_target(const typename D::T* rp, int n, 
     constexpr int NV = 4;
     constexpr int NE = NV * E;
     const int lane = threadIdx.x % kWave;
-    const bool fast = vec_loadable(rp);
     float z[NV][E], zq[NV][E];
-    load_pair_u<D, NV>(rp, rp, false, fast, lane * NV, 1, n, z, zq);
+    load_pair_u<D, NV>(rp, rp, false, lane * NV, 1, n, z, zq);
     // the weights are recomputed where needed rather than kept (registers)
     double sum = 0.0;
 #pragma unroll

@@ -1567,38 +1567,60 @@ __device__ __forceinline__ int wave_find_target(const typename D::T* rp, int n, 
     return wave_max_int(mine);
 }
 
-// Probe outputs of a bonus draw: the draw's total (exact mode in units of the
-// row normaliser, 1 up to rounding; sigmoid mode the plain sum of p_hat) and
-// the row's weights (exact p(x), sigmoid p_hat(x)).
+// The mass probe of a bonus draw: the draw's total (exact mode in units of the
+// row normaliser, 1 up to rounding; sigmoid mode the plain sum of p_hat).
+template <bool kExact>
+__device__ __forceinline__ void bonus_mass_probe(const StepParams& P, int b, float km, double total, bool bad) {
+    const double lam = (double)km + log2(total);  // exact: the row's log2-normaliser
+    P.mass_out[b] = bad ? __builtin_nan("") : (kExact ? total * exp2((double)km - lam) : total);
+}
+
+// The weights probe of a bonus draw: the row's weights (exact p(x), sigmoid
+// p_hat(x)), written by the whole workgroup.  One workgroup per element pays
+// its round trips to memory in sequence, so it keeps kWeightUnroll 16-byte
+// loads per thread in flight.
+constexpr int kWeightUnroll = 8;
 template <class D, bool kExact>
-__device__ __forceinline__ void bonus_probes(const StepParams& P, int b, int gb, float km, double total, bool bad,
-                                             int t0, int nt) {
+__device__ __forceinline__ void bonus_weights_probe(const StepParams& P, int b, int gb, float km, double total) {
     using T = typename D::T;
-    const int gamma = P.gamma, V = P.V;
-    auto lam = [&]() { return (double)km + log2(total); };  // exact: the row's log2-normaliser
-    if (P.mass_out != nullptr && (int)threadIdx.x == 0)
-        P.mass_out[b] = bad ? __builtin_nan("") : (kExact ? total * exp2((double)km - lam()) : total);
-    if (P.weight_out != nullptr && !bad) {
-        const T* rp = static_cast<const T*>(P.target) + ((size_t)b * (gamma + 1) + gb) * V;
-        if constexpr (kExact) {
-            ExactWeights w{};
-            w.kind = kTargetRow;
-            w.c = P.c;
-            split3(lam(), w.kp, w.lp_hi, w.lp_lo);
-            for (int x = t0; x < V; x += nt) P.weight_out[(size_t)b * V + x] = w.template eval<kTargetRow>(to_f32(rp[x]), -INFINITY);
-        } else {
-            const SigmoidWeights w = BonusWeights<false>::of(P, 0.0f);
-            for (int x = t0; x < V; x += nt) P.weight_out[(size_t)b * V + x] = w.template eval<kTargetRow>(to_f32(rp[x]), -INFINITY);
+    constexpr int E = D::E;
+    const int V = P.V;
+    const T* rp = static_cast<const T*>(P.target) + ((size_t)b * (P.gamma + 1) + gb) * V;
+    float* out = P.weight_out + (size_t)b * V;
+    auto wt = BonusWeights<kExact>::of(P, 0.0f);
+    if constexpr (kExact) split3((double)km + log2(total), wt.kp, wt.lp_hi, wt.lp_lo);
+    const int nfull = V / E;
+    for (int v0 = (int)threadIdx.x; v0 < nfull; v0 += kWeightUnroll * kThreads) {
+        u32x4 raw[kWeightUnroll];
+#pragma unroll
+        for (int u = 0; u < kWeightUnroll; ++u) raw[u] = load_vec_or_pad<D, false>(rp, v0 + u * kThreads, nfull);
+#pragma unroll
+        for (int u = 0; u < kWeightUnroll; ++u) {
+            const int v = v0 + u * kThreads;
+            float z[E];
+            unpack<D>(raw[u], z);
+#pragma unroll
+            for (int e = 0; e < E; e += 4) {
+                const u32x4 a = {__float_as_uint(wt.template eval<kTargetRow>(z[e], -INFINITY)),
+                                 __float_as_uint(wt.template eval<kTargetRow>(z[e + 1], -INFINITY)),
+                                 __float_as_uint(wt.template eval<kTargetRow>(z[e + 2], -INFINITY)),
+                                 __float_as_uint(wt.template eval<kTargetRow>(z[e + 3], -INFINITY))};
+                if (v < nfull) *reinterpret_cast<u32x4_el*>(out + (size_t)v * E + e) = a;
+            }
         }
     }
+    for (int x = nfull * E + (int)threadIdx.x; x < V; x += kThreads)
+        out[x] = wt.template eval<kTargetRow>(to_f32(rp[x]), -INFINITY);
 }
 
 // The bonus draw of b by one wave, when target row gamma has at most kWave
 // quarters (see bonus_role): the same steps as the workgroup version, with
 // every value in registers and no workgroup barrier, since this chain ends
-// the step.  The other waves of the workgroup return at once.
+// the step.  The other waves of the workgroup return at once, unless the
+// weights probe wants them: for it wave 0 leaves in sm whether b draws here
+// (result) and the row's scale and total.
 template <class D, bool kExact, bool kRagged, bool kPipe = false>
-__device__ __forceinline__ void bonus_wave_role(const StepParams& P, int b) {
+__device__ __forceinline__ void bonus_wave_role(const StepParams& P, int b, Smem& sm) {
     using T = typename D::T;
     if (threadIdx.x >= kWave) return;
     const int gamma = P.gamma, V = P.V, R = 2 * gamma + 1;
@@ -1702,13 +1724,17 @@ __device__ __forceinline__ void bonus_wave_role(const StepParams& P, int b) {
     if (!(ok && rok) && lane == 0) set_error(P);
     const unsigned long long w0 = ~lane_u64(rw, 0);
     const bool draw = !rok || (((w0 >> 16) & 1) == 0 && (int)(w0 & 0xffff) == gb);
-    if (!draw) return;
     const bool bad = !(ok && rok) || sticky || idx < 0;
-    if (lane == 0) {
+    if (draw && lane == 0) {
         P.accepted_len[b] = bad ? -1 : gb;
         P.next_token[b] = bad ? -1 : idx;
+        if (P.mass_out != nullptr) bonus_mass_probe<kExact>(P, b, km, total, bad);
     }
-    bonus_probes<D, kExact>(P, b, gb, km, total, bad, lane, kWave);
+    if (P.weight_out != nullptr && lane == 0) {
+        sm.result = (draw && !bad) ? 1 : 0;
+        sm.kmax = km;
+        sm.cross_tot = total;
+    }
 }
 
 // b's bonus workgroup: waits for target row gamma's stats (exact mode; they
@@ -1726,11 +1752,15 @@ __device__ __forceinline__ void bonus_role(const StepParams& P, int b, Smem& sm)
     const int gamma = P.gamma, V = P.V, R = 2 * gamma + 1;
     const int tid = threadIdx.x;
     const int W = kWaves * P.nchunkg;  // quarters of the row's tiles
+    bool gbad;
     if (W <= kWave) {
-        bonus_wave_role<D, kExact, kRagged, kPipe>(P, b);
+        bonus_wave_role<D, kExact, kRagged, kPipe>(P, b, sm);
+        if (P.weight_out == nullptr) return;
+        __syncthreads();
+        if (sm.result != 0)
+            bonus_weights_probe<D, kExact>(P, b, elem_gamma<kRagged>(P, b, &gbad), sm.kmax, sm.cross_tot);
         return;
     }
-    bool gbad;
     const int gb = elem_gamma<kRagged>(P, b, &gbad);  // the row drawn from: target row gb
     const double u = (double)P.uniforms[(size_t)b * (gamma + 1) + gb];
     unsigned long long* rec = P.dslot + ((size_t)b * P.ncopy + P.ncopy - 1) * kDecisionWords;
@@ -1804,8 +1834,9 @@ __device__ __forceinline__ void bonus_role(const StepParams& P, int b, Smem& sm)
     if (tid == 0) {
         P.accepted_len[b] = bad ? -1 : gb;
         P.next_token[b] = bad ? -1 : idx;
+        if (P.mass_out != nullptr) bonus_mass_probe<kExact>(P, b, km, total, bad);
     }
-    bonus_probes<D, kExact>(P, b, gb, km, total, bad, tid, kThreads);
+    if (P.weight_out != nullptr && !bad) bonus_weights_probe<D, kExact>(P, b, gb, km, total);
 }
 
 // b's decision for a mass or draw workgroup: in the exact mode the copy

@@ -2302,6 +2302,19 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t n) {
         p[i] = 0u;
 }
 
+// The decoding loop's results for the host: the outputs and the workspace's
+// error flag, stored straight into pinned host memory.  One launch where three
+// small copies each cost the host a call and the stream a transfer.
+__global__ void collect_kernel(const int32_t* accepted_len, const int32_t* next_token, const unsigned int* flag, int B,
+                               int32_t* host_out, uint32_t* host_flag) {
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < B) {
+        host_out[i] = accepted_len[i];
+        host_out[B + i] = next_token[i];
+    }
+    if (i == 0) *host_flag = *flag;
+}
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -2422,6 +2435,15 @@ static void* static_workspace(hipStream_t stream, sv_status_t* st) {
     }
     *st = SV_OK;
     return g_scratch_ptr[dev];
+}
+
+sv_status_t launch_collect(const int32_t* accepted_len, const int32_t* next_token, const void* ws, int32_t B,
+                           int32_t* host_out, uint32_t* host_flag, hipStream_t stream) {
+    const unsigned int* header = static_cast<const unsigned int*>(ws);
+    hipLaunchKernelGGL(collect_kernel, dim3((unsigned int)ceil_div(B, kThreads)), dim3(kThreads), 0, stream,
+                       accepted_len, next_token, header + kErrorFlagOffset / sizeof(unsigned int), B, host_out,
+                       host_flag);
+    return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 
 static sv_status_t run(const Call& a, bool exact) {

@@ -309,17 +309,18 @@ sv_status_t spec_verify_sigmoid_ragged(const void* draft_logits, const void* tar
  * dense tensors of spec_verify_exact / spec_verify_sigmoid at that gamma
  * (draft [B, gamma, V] at `draft`, target [B, gamma+1, V] at `target`,
  * tokens [B, gamma], uniforms [B, gamma+1]), on `stream` or ordered before
- * it.  spec_verify_loop_step then runs the step, copies accepted_len and
- * next_token into `host_out` (pinned host memory, [2B] int32: the accepted
- * lengths, then the next tokens), WAITS for the stream to finish (the host
- * needs L to choose the next gamma and the tokens to append), and writes the
- * next gamma.  With use_graphs the step and the three copies are captured
- * into a HIP graph the first time each gamma is used and replayed afterwards
+ * it.  spec_verify_loop_step then runs the step, collects accepted_len and
+ * next_token in pinned memory of the loop's own, WAITS until they are there
+ * (the host needs L to choose the next gamma and the tokens to append; they are
+ * stored after everything the step and the work before it on the stream do),
+ * copies them into `host_out` (host memory, [2B] int32: the accepted lengths,
+ * then the next tokens), and writes the next gamma.  With use_graphs the step
+ * and the collection are captured into a HIP graph the first time each gamma is used and replayed afterwards
  * (on ROCm 7 replaying this one-kernel graph measured slower than launching
  * it directly, so direct launch is the better default).
  *
- * After the wait the step also reads the workspace's sticky error flag (copied
- * to pinned memory with the outputs) and returns SV_ERR_TIMEOUT, leaving
+ * After the wait the step also reads the workspace's sticky error flag
+ * (collected with the outputs) and returns SV_ERR_TIMEOUT, leaving
  * *next_gamma unwritten, if it is set.
  *
  * Early exit (exact mode; Sec. 3.1 stops at the first rejection):
@@ -334,8 +335,8 @@ sv_status_t spec_verify_sigmoid_ragged(const void* draft_logits, const void* tar
  *
  * Ownership: every pointer in the descriptor is the caller's and must stay
  * valid until spec_verify_loop_destroy; the loop allocates only its host
- * object, one pinned 4-byte word for the flag (at the first step) and the
- * graphs.  The workspace must hold
+ * object, a pinned block of 2B + 2 words for what it collects (at the first
+ * step) and the graphs.  The workspace must hold
  * spec_verify_workspace_bytes(batch, g, vocab, dtype) for every g up to
  * gamma_max (zero-filled before the first iteration; each iteration leaves it
  * zero-filled).  One loop must not be stepped from two threads at once.
@@ -356,7 +357,7 @@ typedef struct sv_loop_desc {
     float* uniforms;              /* device, B * (gamma_max + 1) */
     int32_t* accepted_len;        /* device [B] */
     int32_t* next_token;          /* device [B] */
-    int32_t* host_out;            /* pinned host [2B] */
+    int32_t* host_out;            /* host [2B] */
     void* workspace;
     size_t workspace_bytes;
     hipStream_t stream;

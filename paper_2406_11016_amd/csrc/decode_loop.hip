@@ -1,8 +1,8 @@
 // A decoding loop around the fused verification step: one call per
 // iteration replays the step for the iteration's number of drafts from a
-// HIP graph captured once per gamma (the verification followed by the copy of
-// the accepted lengths and next tokens to pinned host memory), waits for it,
-// and returns the next gamma by the draft-length rule of the paper's
+// HIP graph captured once per gamma (the verification followed by a kernel that
+// stores the accepted lengths and next tokens in pinned host memory), waits for
+// them, and returns the next gamma by the draft-length rule of the paper's
 // experiments (Sec. 4, hyperparameters: gamma starts at 5, grows by 2 after
 // an iteration that accepts every draft, otherwise shrinks by 1; here kept
 // within 1 .. gamma_max, and with several batch elements every element must
@@ -12,15 +12,16 @@
 // (Sec. 3.1 stops at the first rejection): as the descriptor says, or chosen
 // from the previous step's acceptance (early_exit_pays).
 //
-// Host code only: the device work is the library's verification kernel and a
-// kernel that stores its results in pinned host memory (three copies where the
-// device cannot reach host_out).  All device and pinned buffers belong to the
-// caller; the loop object holds the descriptor, one pinned word for the
-// workspace's error flag and the instantiated graphs.
+// Host code only: the device work is the library's verification kernel and the
+// kernel that collects its results.  All device buffers and host_out belong to
+// the caller; the loop object holds the descriptor, a pinned block for the
+// collected results and the instantiated graphs.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <chrono>
+#include <cstring>
 #include <new>
 #include <vector>
 
@@ -29,9 +30,8 @@
 
 struct sv_loop {
     sv_loop_desc_t d;
-    uint32_t* flag = nullptr;          // pinned: the workspace's sticky error flag (from the first step on)
-    uint32_t* flag_dev = nullptr;      // the device's addresses of it and of host_out; null where the
-    int32_t* host_dev = nullptr;       // device cannot reach host_out
+    uint32_t* host = nullptr;          // pinned { done, error flag, outputs [2B] } (from the first step on)
+    uint32_t* host_dev = nullptr;      // the device's address of it
     std::vector<hipGraphExec_t> exec;  // by 2 gamma + early exit (0, 1 unused); null until first use
     bool early = false;                // the next step's choice (exact mode)
     int32_t last_early = -1;           // the last step's choice
@@ -39,20 +39,26 @@ struct sv_loop {
 
 namespace {
 
-// The device's address of pinned host memory, or null if p is not that.
-template <class T>
-T* device_address(T* p) {
-    hipPointerAttribute_t attr{};
-    if (hipPointerGetAttributes(&attr, p) != hipSuccess) {
-        (void)hipGetLastError();  // ordinary host memory: no error of the step
-        return nullptr;
-    }
-    return attr.type == hipMemoryTypeHost ? static_cast<T*>(attr.devicePointer) : nullptr;
+// The collected results have arrived: a poll of the done word, by time, since
+// waiting for the stream costs the runtime's wake-up on top of the work (28.6
+// against 24.2 an iteration, B = 1, V = 51,865 fp32).  The bound is several
+// times the largest step's own time; what takes longer (a producer's work still
+// ahead on the stream, a device that failed) is left to the stream's wait.
+bool arrived(const uint32_t* done) {
+    constexpr auto kSpin = std::chrono::microseconds(200);
+    const auto end = std::chrono::steady_clock::now() + kSpin;
+    do {
+        for (int i = 0; i < 32; ++i) {
+            if (__atomic_load_n(done, __ATOMIC_ACQUIRE) != 0u) return true;
+            __builtin_ia32_pause();
+        }
+    } while (std::chrono::steady_clock::now() < end);
+    return false;
 }
 
 // The verification of the leading [B, gamma, V] parts of the static buffers
-// and the copy of its outputs to host_out and of the workspace's error flag,
-// enqueued on the loop's stream.
+// and the collection of its outputs and of the workspace's error flag, enqueued
+// on the loop's stream.
 sv_status_t enqueue(const sv_loop* loop, int32_t gamma, bool early) {
     const sv_loop_desc_t& d = loop->d;
     sv_status_t st;
@@ -69,17 +75,7 @@ sv_status_t enqueue(const sv_loop* loop, int32_t gamma, bool early) {
                                  d.temperature, d.alpha, d.beta, d.accepted_len, d.next_token, d.workspace,
                                  d.workspace_bytes, d.stream);
     if (st != SV_OK) return st;
-    // (B = 1, V = 51,865 fp32: 31.8 us an iteration with three copies)
-    if (loop->host_dev != nullptr && loop->flag_dev != nullptr)
-        return sv::launch_collect(d.accepted_len, d.next_token, d.workspace, d.batch, loop->host_dev, loop->flag_dev,
-                                  d.stream);
-    const size_t n = sizeof(int32_t) * (size_t)d.batch;
-    if (hipMemcpyAsync(d.host_out, d.accepted_len, n, hipMemcpyDeviceToHost, d.stream) != hipSuccess ||
-        hipMemcpyAsync(d.host_out + d.batch, d.next_token, n, hipMemcpyDeviceToHost, d.stream) != hipSuccess ||
-        hipMemcpyAsync(loop->flag, static_cast<const char*>(d.workspace) + sv::kErrorFlagOffset, sizeof(uint32_t),
-                       hipMemcpyDeviceToHost, d.stream) != hipSuccess)
-        return SV_ERR_HIP;
-    return SV_OK;
+    return sv::launch_collect(d.accepted_len, d.next_token, d.workspace, d.batch, loop->host_dev, d.stream);
 }
 
 sv_status_t capture(sv_loop* loop, int32_t gamma, bool early) {
@@ -131,17 +127,24 @@ sv_status_t spec_verify_loop_step(sv_loop* loop, int32_t gamma, int32_t* next_ga
     if (loop == nullptr || next_gamma == nullptr) return SV_ERR_NULL;
     const sv_loop_desc_t& d = loop->d;
     if (gamma < 1 || gamma > d.gamma_max) return SV_ERR_PARAM;
-    if (loop->flag == nullptr) {
-        // the pinned word the flag is copied to, allocated once (a step needs
-        // the GPU anyway; creating the loop does not)
-        void* flag = nullptr;
-        if (hipHostMalloc(&flag, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess || flag == nullptr)
+    if (loop->host == nullptr) {
+        // allocated once, here (a step needs the GPU anyway; creating the loop
+        // does not); coherent, since the host reads it while the kernel runs
+        void *host = nullptr, *dev = nullptr;
+        if (hipHostMalloc(&host, sizeof(uint32_t) * (2 + 2 * (size_t)d.batch), hipHostMallocCoherent) != hipSuccess ||
+            host == nullptr)
             return SV_ERR_HIP;
-        loop->flag = static_cast<uint32_t*>(flag);
-        loop->flag_dev = device_address(loop->flag);
-        loop->host_dev = device_address(d.host_out);
+        if (hipHostGetDevicePointer(&dev, host, 0) != hipSuccess || dev == nullptr) {
+            (void)hipHostFree(host);
+            return SV_ERR_HIP;
+        }
+        loop->host = static_cast<uint32_t*>(host);
+        loop->host_dev = static_cast<uint32_t*>(dev);
     }
-    *loop->flag = 0;
+    // No earlier step's kernel can still store here: each step returns after its
+    // done word or after the stream's wait.
+    loop->host[1] = 0;
+    __atomic_store_n(loop->host, 0u, __ATOMIC_RELEASE);
     const bool early = loop->early;
     if (d.use_graphs) {
         hipGraphExec_t& e = loop->exec[2 * gamma + (early ? 1 : 0)];
@@ -155,8 +158,10 @@ sv_status_t spec_verify_loop_step(sv_loop* loop, int32_t gamma, int32_t* next_ga
         if (st != SV_OK) return st;
     }
     loop->last_early = (d.mode == 0 && early) ? 1 : 0;
-    if (hipStreamSynchronize(d.stream) != hipSuccess) return SV_ERR_HIP;
-    if (*loop->flag != 0) return SV_ERR_TIMEOUT;
+    // (a replayed graph is waited for whole: destroying the loop frees it)
+    if ((d.use_graphs || !arrived(loop->host)) && hipStreamSynchronize(d.stream) != hipSuccess) return SV_ERR_HIP;
+    std::memcpy(d.host_out, loop->host + 2, sizeof(int32_t) * 2 * (size_t)d.batch);
+    if (loop->host[1] != 0) return SV_ERR_TIMEOUT;
     bool all = true;
     long long accepted = 0;
     for (int32_t b = 0; b < d.batch; ++b) {
@@ -175,7 +180,7 @@ sv_status_t spec_verify_loop_destroy(sv_loop* loop) {
     sv_status_t st = SV_OK;
     for (hipGraphExec_t e : loop->exec)
         if (e != nullptr && hipGraphExecDestroy(e) != hipSuccess) st = SV_ERR_HIP;
-    if (loop->flag != nullptr && hipHostFree(loop->flag) != hipSuccess) st = SV_ERR_HIP;
+    if (loop->host != nullptr && hipHostFree(loop->host) != hipSuccess) st = SV_ERR_HIP;
     delete loop;
     return st;
 }

@@ -456,10 +456,10 @@ inline sv_status_t validate(const Call& a, bool exact, Plan* pl) {
     return SV_OK;
 }
 
-// Copies the B accepted lengths and next tokens to host_out and the
-// workspace's error flag to host_flag (both pinned host memory, at the
-// addresses the device uses) with one kernel on `stream`.
+// Stores { 1, the workspace's error flag, the B accepted lengths, the B next
+// tokens } in `host` (coherent pinned memory, at the address the device uses)
+// with one kernel on `stream`; the leading 1 is released after all the others.
 sv_status_t launch_collect(const int32_t* accepted_len, const int32_t* next_token, const void* ws, int32_t B,
-                           int32_t* host_out, uint32_t* host_flag, hipStream_t stream);
+                           uint32_t* host, hipStream_t stream);
 
 }  // namespace sv

@@ -2302,17 +2302,24 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t n) {
         p[i] = 0u;
 }
 
-// The decoding loop's results for the host: the outputs and the workspace's
-// error flag, stored straight into pinned host memory.  One launch where three
-// small copies each cost the host a call and the stream a transfer.
+// The decoding loop's results for the host: { done, error flag, B accepted
+// lengths, B next tokens } in coherent pinned memory, done last, which the host
+// polls.  One workgroup, so that one barrier orders every store before it: each
+// thread's fence covers its own stores, whichever wave they are in.  Bound by
+// the launch and the transfer of a few words; three small copies and a wait for
+// the stream in its place cost 31.6 us an iteration against 24.2 (B = 1,
+// V = 51,865 fp32).
 __global__ void collect_kernel(const int32_t* accepted_len, const int32_t* next_token, const unsigned int* flag, int B,
-                               int32_t* host_out, uint32_t* host_flag) {
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i < B) {
-        host_out[i] = accepted_len[i];
-        host_out[B + i] = next_token[i];
+                               uint32_t* host) {
+    int32_t* out = reinterpret_cast<int32_t*>(host + 2);
+    for (int i = (int)threadIdx.x; i < B; i += kThreads) {
+        out[i] = accepted_len[i];
+        out[(size_t)B + i] = next_token[i];
     }
-    if (i == 0) *host_flag = *flag;
+    if (threadIdx.x == 0) host[1] = *flag;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(host, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------------------
@@ -2438,11 +2445,10 @@ static void* static_workspace(hipStream_t stream, sv_status_t* st) {
 }
 
 sv_status_t launch_collect(const int32_t* accepted_len, const int32_t* next_token, const void* ws, int32_t B,
-                           int32_t* host_out, uint32_t* host_flag, hipStream_t stream) {
+                           uint32_t* host, hipStream_t stream) {
     const unsigned int* header = static_cast<const unsigned int*>(ws);
-    hipLaunchKernelGGL(collect_kernel, dim3((unsigned int)ceil_div(B, kThreads)), dim3(kThreads), 0, stream,
-                       accepted_len, next_token, header + kErrorFlagOffset / sizeof(unsigned int), B, host_out,
-                       host_flag);
+    hipLaunchKernelGGL(collect_kernel, dim3(1), dim3(kThreads), 0, stream, accepted_len, next_token,
+                       header + kErrorFlagOffset / sizeof(unsigned int), B, host);
     return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_HIP;
 }
 

@@ -13,10 +13,11 @@ The loop owns static device buffers sized for ``gamma_max``.  Whatever
 produces the logits (the draft and target models of a decoder; a synthetic
 source here) writes an iteration's ``[B, gamma, V]`` / ``[B, gamma + 1, V]``
 logits, drafted tokens and uniforms into the leading part of those buffers;
-an iteration then costs one launch of the step, three small device-to-host
-copies into pinned memory (the accepted lengths, the next tokens and the
-workspace's error flag) and one stream synchronisation -- the host needs the
-accepted length to decide the next gamma and which tokens to append.  With
+an iteration then costs one launch of the step, the transfer of its results
+(the accepted lengths, the next tokens and the workspace's error flag) to
+pinned memory -- three small copies here, one kernel in the native loop -- and
+one wait for them: the host needs the accepted length to decide the next gamma
+and which tokens to append.  With
 ``use_graphs`` the call for each gamma is captured once into a HIP graph
 (lazily, on first use) and replayed instead; on ROCm 7 that measured slower
 than launching this one-kernel step directly, so it is off by default.
@@ -105,7 +106,7 @@ class DecodeLoop:
         self.stream = torch.cuda.Stream(self.device)
         self.graphs: Dict[Tuple[int, bool], torch.cuda.CUDAGraph] = {}
         # the native loop: one library call per iteration (graph replay or
-        # launch, the copies to pinned memory, the wait and the gamma rule)
+        # launch, the transfer of the results, the wait and the gamma rule)
         self.native = None
         if native:
             desc = binding.LoopDesc(

@@ -32,6 +32,7 @@ constexpr int kWantSampleTiles = 1024;
 constexpr int kStatsTileBytes = 32768;   // at most 32 KiB of one row per stats workgroup
 constexpr long long kSelfDecideWords = 16384;     // pair copies polled by self-deciding mass workgroups
 constexpr long long kLagStreamBytes = 56000000;  // stream between an element's stats and its mass tiles
+constexpr long long kRaggedLagBytes = 42000000;  // the same in the ragged variant, in bytes it can be expected to read
 constexpr int kGammaTileBytes = 16384;   // target rows gamma, streamed last: short tiles end the stream sharply
 constexpr int kSampleTileBytes = 32768;
 constexpr int kMaxStatsSub = 1028;       // stats chunks of one batch element's 2 gamma decision rows
@@ -198,10 +199,16 @@ struct Layout {
 // The lag in units: about kLagStreamBytes of stream (~9 us at 6.5 TB/s, the
 // time a decision takes to publish under load) behind the element's stats,
 // and all of them after the stream when the whole stream is shorter than
-// that (or absent: the sigmoid mode streams no rows).
-inline long long lag_units(long long B, long long unit_bytes) {
+// that (or absent: the sigmoid mode streams no rows).  A longer lag is quicker
+// where many elements reject (their mass tiles' loads queue behind the stream)
+// and slower where few do and one of them is late (its residual then comes
+// after the stream): means over 10 and 12 seeds of lags 56 / 84 / 126 MB at
+// B = 64, V = 128,256 bf16: gamma 8, noise 1 59.6 / 59.0 / 58.4 us, gamma 8 of
+// nearly right drafts 50.2 / 50.7 / 51.1 (one seed 45.8 / 50.1 / 50.2), gamma
+// 20 of them 103.9 / 105.9 / 106.5.  28 MB is slower on every shape.
+inline long long lag_units(long long B, long long unit_bytes, long long lag_bytes = kLagStreamBytes) {
     if (unit_bytes <= 0) return B;
-    return std::min(B, std::max(1LL, ceil_div(kLagStreamBytes, unit_bytes)));
+    return std::min(B, std::max(1LL, ceil_div(lag_bytes, unit_bytes)));
 }
 
 inline Layout make_layout(long long B, long long S, long long Mt, long long G, int nchunk1, int nchunkg,
@@ -308,10 +315,22 @@ constexpr Role role_at(const Layout& y, int nchunk1, int nchunkg, unsigned int i
 // decision rows' stats tiles; target row gamma (exact: stats tiles, sigmoid:
 // row tiles) after the units; the lag from kLagStreamBytes of decision-row
 // stream.  The grid has end2 + B workgroups (the bonus workgroups last).
-inline Layout single_pass_layout(long long B, long long gamma, long long V, sv_dtype_t dt, bool exact, const Plan& pl) {
-    const long long unit_bytes = exact ? 2LL * gamma * V * bytes_per_logit(dt) : 0;
+//
+// In the ragged variant a unit streams the rows of its element's own drafts,
+// which only the device knows: gamma + 1 rows in the mean if every number of
+// drafts is as likely.  Counted as 2 gamma rows, as before, the mass tiles came
+// too early; kRaggedLagBytes is the longest lag that no law measured loses by.
+// Means over 8 seeds, 2 gamma rows and 56 MB, then gamma + 1 rows and 42 / 56
+// MB, us:
+//   B = 30, gamma 20, V = 65,001 bf16   noise 1: 33.0, 31.6 / 30.7; nearly right drafts: 30.3, 29.3 / 28.8
+//   B = 32, gamma 10, V = 51,865 fp32   noise 1: 26.9, 26.0 / 25.2; nearly right drafts: 24.1, 23.4 / 23.1
+//   B = 64, gamma 8,  V = 128,256 bf16  noise 1: 47.5, 46.8 / 46.3; nearly right drafts: 37.3, 37.3 / 38.2
+//   B = 110, gamma 2, V = 100,000 bf16  noise 1: 34.2, 34.2 / 32.9; nearly right drafts: 28.2, 28.2 / 27.9
+inline Layout single_pass_layout(long long B, long long gamma, long long V, sv_dtype_t dt, bool exact, const Plan& pl,
+                                 bool ragged = false) {
+    const long long unit_bytes = exact ? (ragged ? gamma + 1 : 2LL * gamma) * V * bytes_per_logit(dt) : 0;
     return make_layout(B, exact ? 2LL * gamma * pl.nchunk1 : 0, pl.nchunk2, B * pl.nchunkg, pl.nchunk1, pl.nchunkg,
-                       lag_units(B, unit_bytes));
+                       lag_units(B, unit_bytes, ragged ? kRaggedLagBytes : kLagStreamBytes));
 }
 
 // Whether the single pass (exact mode, not ragged) waits with two polls in

@@ -1577,8 +1577,11 @@ __device__ __forceinline__ void bonus_mass_probe(const StepParams& P, int b, flo
 
 // The weights probe of a bonus draw: the row's weights (exact p(x), sigmoid
 // p_hat(x)), written by the whole workgroup.  One workgroup per element pays
-// its round trips to memory in sequence, so it keeps kWeightUnroll 16-byte
-// loads per thread in flight.
+// its round trips to memory in sequence, which bounds it, so it keeps
+// kWeightUnroll 16-byte loads per thread in flight: a step of B = 16, gamma 5,
+// V = 51,865 fp32 with all probes 33 us, of which the kernel 23.4 and the
+// fills of the probe tensors most of the rest (312 us with one wave storing an
+// element per lane at a time; 15.5 us without probes).
 constexpr int kWeightUnroll = 8;
 template <class D, bool kExact>
 __device__ __forceinline__ void bonus_weights_probe(const StepParams& P, int b, int gb, float km, double total) {

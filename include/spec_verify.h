@@ -342,7 +342,10 @@ sv_status_t spec_verify_sigmoid_ragged(const void* draft_logits, const void* tar
  * zero-filled).  One loop must not be stepped from two threads at once.
  * Errors: SV_ERR_NULL, SV_ERR_SHAPE, SV_ERR_PARAM (mode not 0/1, early_exit
  * not 0-2, gamma out of 1 .. gamma_max), SV_ERR_WORKSPACE, SV_ERR_ALLOC at creation; the
- * verification's own errors, SV_ERR_HIP and SV_ERR_TIMEOUT at a step.
+ * verification's own errors, SV_ERR_HIP and SV_ERR_TIMEOUT at a step.  A step
+ * that failed may have left work on the stream: the next step, or the
+ * destruction, waits for it first, and returns SV_ERR_HIP if it cannot (a
+ * destruction then leaves the pinned block and the graphs allocated).
  */
 typedef struct sv_loop sv_loop;
 

@@ -33,6 +33,7 @@ struct sv_loop {
     uint32_t* host = nullptr;          // pinned { done, error flag, outputs [2B] } (from the first step on)
     uint32_t* host_dev = nullptr;      // the device's address of it
     std::vector<hipGraphExec_t> exec;  // by 2 gamma + early exit (0, 1 unused); null until first use
+    bool settled = true;               // nothing that a step enqueued can still store in the block
     bool early = false;                // the next step's choice (exact mode)
     int32_t last_early = -1;           // the last step's choice
 };
@@ -141,8 +142,12 @@ sv_status_t spec_verify_loop_step(sv_loop* loop, int32_t gamma, int32_t* next_ga
         loop->host = static_cast<uint32_t*>(host);
         loop->host_dev = static_cast<uint32_t*>(dev);
     }
-    // No earlier step's kernel can still store here: each step returns after its
-    // done word or after the stream's wait.
+    // An earlier step that failed (its enqueueing, or the wait) may have left its
+    // kernels on the stream, whose done word would pass for this step's: they
+    // are waited for first.  Every other step ended after its done word or after
+    // the stream's wait.
+    if (!loop->settled && hipStreamSynchronize(d.stream) != hipSuccess) return SV_ERR_HIP;
+    loop->settled = false;
     loop->host[1] = 0;
     __atomic_store_n(loop->host, 0u, __ATOMIC_RELEASE);
     const bool early = loop->early;
@@ -160,6 +165,7 @@ sv_status_t spec_verify_loop_step(sv_loop* loop, int32_t gamma, int32_t* next_ga
     loop->last_early = (d.mode == 0 && early) ? 1 : 0;
     // (a replayed graph is waited for whole: destroying the loop frees it)
     if ((d.use_graphs || !arrived(loop->host)) && hipStreamSynchronize(d.stream) != hipSuccess) return SV_ERR_HIP;
+    loop->settled = true;
     std::memcpy(d.host_out, loop->host + 2, sizeof(int32_t) * 2 * (size_t)d.batch);
     if (loop->host[1] != 0) return SV_ERR_TIMEOUT;
     bool all = true;
@@ -178,6 +184,11 @@ int32_t spec_verify_loop_last_early_exit(const sv_loop* loop) { return loop == n
 sv_status_t spec_verify_loop_destroy(sv_loop* loop) {
     if (loop == nullptr) return SV_OK;
     sv_status_t st = SV_OK;
+    if (!loop->settled && hipStreamSynchronize(loop->d.stream) != hipSuccess) {
+        // a failed step's kernels may still run: what they use is left allocated
+        delete loop;
+        return SV_ERR_HIP;
+    }
     for (hipGraphExec_t e : loop->exec)
         if (e != nullptr && hipGraphExecDestroy(e) != hipSuccess) st = SV_ERR_HIP;
     if (loop->host != nullptr && hipHostFree(loop->host) != hipSuccess) st = SV_ERR_HIP;

@@ -32,7 +32,6 @@ constexpr int kWantSampleTiles = 1024;
 constexpr int kStatsTileBytes = 32768;   // at most 32 KiB of one row per stats workgroup
 constexpr long long kSelfDecideWords = 16384;     // pair copies polled by self-deciding mass workgroups
 constexpr long long kLagStreamBytes = 56000000;  // stream between an element's stats and its mass tiles
-constexpr long long kRaggedLagBytes = 42000000;  // the same in the ragged variant, in bytes it can be expected to read
 constexpr int kGammaTileBytes = 16384;   // target rows gamma, streamed last: short tiles end the stream sharply
 constexpr int kSampleTileBytes = 32768;
 constexpr int kMaxStatsSub = 1028;       // stats chunks of one batch element's 2 gamma decision rows
@@ -206,9 +205,9 @@ struct Layout {
 // B = 64, V = 128,256 bf16: gamma 8, noise 1 59.6 / 59.0 / 58.4 us, gamma 8 of
 // nearly right drafts 50.2 / 50.7 / 51.1 (one seed 45.8 / 50.1 / 50.2), gamma
 // 20 of them 103.9 / 105.9 / 106.5.  28 MB is slower on every shape.
-inline long long lag_units(long long B, long long unit_bytes, long long lag_bytes = kLagStreamBytes) {
+inline long long lag_units(long long B, long long unit_bytes) {
     if (unit_bytes <= 0) return B;
-    return std::min(B, std::max(1LL, ceil_div(lag_bytes, unit_bytes)));
+    return std::min(B, std::max(1LL, ceil_div(kLagStreamBytes, unit_bytes)));
 }
 
 inline Layout make_layout(long long B, long long S, long long Mt, long long G, int nchunk1, int nchunkg,
@@ -316,21 +315,21 @@ constexpr Role role_at(const Layout& y, int nchunk1, int nchunkg, unsigned int i
 // row tiles) after the units; the lag from kLagStreamBytes of decision-row
 // stream.  The grid has end2 + B workgroups (the bonus workgroups last).
 //
-// In the ragged variant a unit streams the rows of its element's own drafts,
-// which only the device knows: gamma + 1 rows in the mean if every number of
-// drafts is as likely.  Counted as 2 gamma rows, as before, the mass tiles came
-// too early; kRaggedLagBytes is the longest lag that no law measured loses by.
-// Means over 8 seeds, 2 gamma rows and 56 MB, then gamma + 1 rows and 42 / 56
-// MB, us:
-//   B = 30, gamma 20, V = 65,001 bf16   noise 1: 33.0, 31.6 / 30.7; nearly right drafts: 30.3, 29.3 / 28.8
-//   B = 32, gamma 10, V = 51,865 fp32   noise 1: 26.9, 26.0 / 25.2; nearly right drafts: 24.1, 23.4 / 23.1
-//   B = 64, gamma 8,  V = 128,256 bf16  noise 1: 47.5, 46.8 / 46.3; nearly right drafts: 37.3, 37.3 / 38.2
-//   B = 110, gamma 2, V = 100,000 bf16  noise 1: 34.2, 34.2 / 32.9; nearly right drafts: 28.2, 28.2 / 27.9
-inline Layout single_pass_layout(long long B, long long gamma, long long V, sv_dtype_t dt, bool exact, const Plan& pl,
-                                 bool ragged = false) {
-    const long long unit_bytes = exact ? (ragged ? gamma + 1 : 2LL * gamma) * V * bytes_per_logit(dt) : 0;
+// The ragged variant takes the plain call's layout, although a unit streams only
+// the rows of its element's own drafts, which the device alone knows.  Counting
+// a unit as gamma + 1 rows, with a lag of 42 MB (more units from gamma 3 on,
+// fewer at gamma 1), was measured against this rule over 6-20 seeds of three
+// laws on 28 shapes and is not kept, since the host cannot tell its gains from
+// its losses.  Numbers of drafts uniform in 1 .. gamma gain up to 1.5 us from
+// gamma 3 on (B = 64, gamma 8, V = 128,256 bf16 44.8 -> 44.1; B = 30, gamma 20,
+// V = 65,001 bf16 33.0 -> 31.7).  Elements that use all of theirs, nearly right,
+// lose up to 0.7 us where the stream is long (B = 64, gamma 8, V = 80,000 fp32
+// 61.1 -> 61.8; B = 32, gamma 8, V = 256,512 bf16 50.1 -> 50.7), and gamma 1
+// loses 0.1-0.9 us (B = 128, V = 128,256 bf16 36.8 -> 37.7).
+inline Layout single_pass_layout(long long B, long long gamma, long long V, sv_dtype_t dt, bool exact, const Plan& pl) {
+    const long long unit_bytes = exact ? 2LL * gamma * V * bytes_per_logit(dt) : 0;
     return make_layout(B, exact ? 2LL * gamma * pl.nchunk1 : 0, pl.nchunk2, B * pl.nchunkg, pl.nchunk1, pl.nchunkg,
-                       lag_units(B, unit_bytes, ragged ? kRaggedLagBytes : kLagStreamBytes));
+                       lag_units(B, unit_bytes));
 }
 
 // Whether the single pass (exact mode, not ragged) waits with two polls in

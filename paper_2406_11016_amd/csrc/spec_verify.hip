@@ -2350,7 +2350,7 @@ static sv_status_t launch(const Call& a, bool exact, const Plan& pl) {
     P.pstride = (int)pl.pstride;
     P.qstride = (int)pl.qstride;
     P.qslot = reinterpret_cast<unsigned long long*>(ws + pl.off_qslot);
-    P.y = single_pass_layout(a.B, a.gamma, a.V, a.dt, exact, pl, a.gammas != nullptr);
+    P.y = single_pass_layout(a.B, a.gamma, a.V, a.dt, exact, pl);
     const long long n_total = (long long)P.y.end2 + a.B;
     P.temperature = (double)a.temperature;
     P.alpha = (double)a.alpha;

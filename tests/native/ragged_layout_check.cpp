@@ -1,5 +1,6 @@
-// The ragged launch's role order over batches around its lag: every role of
-// every element once, and each after what it waits on.
+// The ragged launch's role order over batches around its lag (the plain call's):
+// every role of every element once, and each after what it waits on.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -16,9 +17,9 @@ static void fail(const char* what, int B, int gamma, int V) {
 static void check(int B, int gamma, int V, sv_dtype_t dt) {
     Plan p{};
     if (!make_plan(B, gamma, V, dt, &p)) fail("no plan", B, gamma, V);
-    const Layout y = single_pass_layout(B, gamma, V, dt, true, p, true);
-    const long long unit = (gamma + 1LL) * V * bytes_per_logit(dt);
-    if (y.lagM != lag_units(B, unit, kRaggedLagBytes) || y.lagM < 1 || y.lagM > B) fail("lag", B, gamma, V);
+    const Layout y = single_pass_layout(B, gamma, V, dt, true, p);
+    const long long unit = 2LL * gamma * V * bytes_per_logit(dt);
+    if (y.lagM != std::min<long long>(B, ceil_div(kLagStreamBytes, unit)) || y.lagM < 1 || y.lagM > B) fail("lag", B, gamma, V);
     const int S = 2 * gamma * p.nchunk1;
     std::vector<long long> last_stats(B, -1), decider(B, -1), draw(B, -1), bonus(B, -1);
     std::vector<int> stats((size_t)B * S), mass((size_t)B * p.nchunk2), rowg((size_t)B * p.nchunkg);
@@ -54,7 +55,7 @@ int main() {
     const struct { int gamma, V; sv_dtype_t dt; } shapes[] = {
         {1, 51865, SV_F32}, {2, 100000, SV_BF16}, {8, 128256, SV_BF16}, {20, 65001, SV_F16}, {7, 131073, SV_F32}, {3, 9, SV_F32}};
     for (const auto& s : shapes) {
-        const long long lag = ceil_div(kRaggedLagBytes, (s.gamma + 1LL) * s.V * bytes_per_logit(s.dt));
+        const long long lag = ceil_div(kLagStreamBytes, 2LL * s.gamma * s.V * bytes_per_logit(s.dt));
         for (long long B : {1LL, 2LL, 9LL, lag - 1, lag, lag + 1, 2 * lag})
             if (B >= 1 && B <= 700) check((int)B, s.gamma, s.V, s.dt);
     }

@@ -98,7 +98,7 @@ def test_short_stream_block_depths(B, gamma, V, dtype):
 @pytest.mark.parametrize("mode", ["exact", "sigmoid"])
 def test_unaligned_rows_and_offsets(mode):
     # odd V in fp32: every row after the first starts off a 16-byte boundary;
-    # odd V in 16-bit storage: rows start off a 4-byte boundary (element loads)
+    # odd V in 16-bit storage: every other row starts off a 4-byte boundary
     for dt, V in (("f32", 12347), ("bf16", 12347), ("f16", 2049)):
         x = W.small_case(7, 4, V, dt, mode=mode, seed=3, alpha=-1e3, beta=1e3)
         compare(x, run_gpu(x), run_oracle(x), label=f"odd V {dt}")

@@ -364,11 +364,10 @@ __device__ __forceinline__ double wave_weight_sum_k(const typename D::T* rp, con
     const int lane = threadIdx.x % kWave;
     const int nvec = (n + E - 1) / E;
     const int nfull = n / E;
-    const bool fast = nfull > 0;
     double acc = 0.0;
     for (int v0 = 0; v0 < nvec; v0 += kPassUnroll * kWave) {
         u32x4 ra[kPassUnroll], rb[kPassUnroll];
-        if (fast) {
+        if (nfull > 0) {
 #pragma unroll
             for (int u = 0; u < kPassUnroll; ++u) {
                 ra[u] = load_vec_or_pad<D, false>(rp, v0 + u * kWave + lane, nfull);
@@ -380,7 +379,7 @@ __device__ __forceinline__ double wave_weight_sum_k(const typename D::T* rp, con
             const int v = v0 + u * kWave + lane;
             if (v >= nvec) continue;
             float zp[E], zq[E];
-            if (fast && v < nfull) {
+            if (v < nfull) {
                 unpack<D>(ra[u], zp);
                 if (two_rows) unpack<D>(rb[u], zq);
             } else {

@@ -310,7 +310,8 @@ def decode_loop(iterations: int, gamma_max: int = 20, pool: int = 32) -> dict:
             runs.append(p)
     return {"sweep": "decode_loop", "gamma0": 5, "gamma_max": gamma_max, "runs": runs,
             "what": "iterations of: copy the next synthetic step's logits into the loop's static buffers, "
-                    "verify, copy L and the next token to pinned host memory, synchronise, apply the gamma rule; "
+                    "verify, bring L and the next token to pinned host memory, wait for them (the python loop and the "
+                    "native graphs for the stream, the native direct launch for its done word), apply the gamma rule; "
                     "python = torch calls per iteration, native = one library call per iteration "
                     "(spec_verify_loop_step); step_device_us only for the python loop"}
 

@@ -315,9 +315,18 @@ sv_status_t spec_verify_sigmoid_ragged(const void* draft_logits, const void* tar
  * stored after everything the step and the work before it on the stream do),
  * copies them into `host_out` (host memory, [2B] int32: the accepted lengths,
  * then the next tokens), and writes the next gamma.  With use_graphs the step
- * and the collection are captured into a HIP graph the first time each gamma is used and replayed afterwards
- * (on ROCm 7 replaying this one-kernel graph measured slower than launching
- * it directly, so direct launch is the better default).
+ * and the collection are captured into a HIP graph the first time each gamma is
+ * used and replayed afterwards (on ROCm 7 replaying a graph of one or two such
+ * kernels measured no faster than launching them directly, so direct launch is
+ * the better default).
+ *
+ * The wait of a direct launch polls for up to 200 us, on the calling thread,
+ * and then waits for the stream; a replayed graph is waited for on the stream.
+ * A returned direct-launch step guarantees its results, and that everything put
+ * on the stream before them has completed, but not that the stream has been
+ * synchronised: the kernel that collects may still be retiring, so the stream
+ * may report busy for a moment, and an error that the device raises then
+ * surfaces at the next wait.
  *
  * After the wait the step also reads the workspace's sticky error flag
  * (collected with the outputs) and returns SV_ERR_TIMEOUT, leaving

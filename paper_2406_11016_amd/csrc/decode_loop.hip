@@ -41,10 +41,13 @@ struct sv_loop {
 namespace {
 
 // The collected results have arrived: a poll of the done word, by time, since
-// waiting for the stream costs the runtime's wake-up on top of the work (28.6
-// against 24.2 an iteration, B = 1, V = 51,865 fp32).  The bound is several
-// times the largest step's own time; what takes longer (a producer's work still
-// ahead on the stream, a device that failed) is left to the stream's wait.
+// waiting for the stream costs the runtime's wake-up on top of the work (28.6 us
+// an iteration against 24.2, B = 1, V = 51,865 fp32, the inputs in place).  The
+// bound is a fixed 200 us from the enqueueing on, for the short steps that the
+// wake-up weighs on.  What takes longer is polled for 200 us and then left to the
+// stream's wait: large steps (B = 64, gamma 20, V = 128,256 bf16 takes 104 us,
+// twice the batch in fp32 four times that), a producer's work still ahead on the
+// stream, a device that failed.
 bool arrived(const uint32_t* done) {
     constexpr auto kSpin = std::chrono::microseconds(200);
     const auto end = std::chrono::steady_clock::now() + kSpin;
